@@ -186,12 +186,12 @@ mvd_status mvd_set_psf(mvd_ctx *ctx, int view, const float *taps, int kz, int kx
                        int back_mode, const float *back_taps);
 
 /* float32_only != 0: this context runs separable kernels of every size on the
- * float32 matrix units.  By default those of 8 to 63 taps run on the 16-bit
- * units on operands split in two, which is faster and nearer to 64 bits but
- * rounds differently; a tap gradient, a sum over every voxel that nearly
- * cancels, shows that in its last digits.  The differentiable path
- * (paper_1503_07998_amd.autograd) keeps to the float32 units.  Captured runs and
- * batches of the context must be made again.  Errors: MVD_ERR_ARG. */
+ * float32 matrix units.  By default those of 8 to 63 taps run on the 16-bit units
+ * where that is faster, on operands in three parts that together hold float32's 24
+ * bits: as near to 64 bits, but rounded differently; a tap gradient, a sum over
+ * every voxel that nearly cancels, shows that in its last digits.  The
+ * differentiable path (paper_1503_07998_amd.autograd) keeps to the float32 units.
+ * Captured runs and batches of the context must be made again.  Errors: MVD_ERR_ARG. */
 mvd_status mvd_set_float32_units(mvd_ctx *ctx, int float32_only);
 
 /* Host copy of the effective back-projector X_v (float32 [kz][kx] of view v's

@@ -115,7 +115,7 @@ __device__ __noinline__ void march_pass(int kind, uint64_t aptr, int b, int t, u
   march::KArg *a = (march::KArg *)(((uint64_t)hi << 32) | lo);
   b = __builtin_amdgcn_readfirstlane(b);
   extern __shared__ __align__(16) float lds_all[];
-  h4 *T = reinterpret_cast<h4 *>(lds_all + __builtin_amdgcn_readfirstlane(lds_off));
+  u32x2 *T = reinterpret_cast<u32x2 *>(lds_all + __builtin_amdgcn_readfirstlane(lds_off));
   const int groups = (a->nstrip + kPqHalfWaves - 1) / kPqHalfWaves;
   const int strip = __builtin_amdgcn_readfirstlane(b % groups * kPqHalfWaves + (t >> 6));
   const int tile = b / groups * a->nstrip + strip;
@@ -123,11 +123,11 @@ __device__ __noinline__ void march_pass(int kind, uint64_t aptr, int b, int t, u
   const int nv = a->nviews;
   struct {
     march::KArg *a;
-    h4 *T;
+    u32x2 *T;
     int nv, t;
-    h2 tap;
+    u32x2 tap;
     __device__ __forceinline__ void taps() {
-      h2 *span = reinterpret_cast<h2 *>(reinterpret_cast<char *>(T) + tap_bytes(H, nv));
+      u32x2 *span = reinterpret_cast<u32x2 *>(reinterpret_cast<char *>(T) + tap_bytes(H, nv));
       if (t < 2 * nv * TapSpan<H>::N) span[t] = tap;
       lds_sync();
       expand_taps<H>(T, span, nv, t, 64 * kPqHalfWaves);

@@ -869,23 +869,9 @@ void fused_geom(SepPassArgs &a, PlaneGeom g, int kb) {
   march_split(a, (long)g.Y * a.nstrip, 256L, 1, 2.5);
 }
 
-// Exponents of one factor: the power of two that puts its largest tap into
-// [2^13, 2^14), and that of a bound on the sum of its absolute values.
-void march_exps(const std::vector<float> &f, int *texp, int *tsum) {
-  double m = 0.0, sum = 0.0;
-  for (float t : f) {
-    m = std::max(m, std::fabs((double)t));
-    sum += std::fabs((double)t);
-  }
-  *texp = m > 0.0 ? std::min(13 - std::ilogb(m), 100) : 0;   // (scales stay normal float32 numbers)
-  *tsum = sum > 0.0 ? (int)std::ceil(std::log2(sum)) : 0;
-}
-
 void march_factors(SepPassArgs &a, int k, const std::vector<float> &fz, const std::vector<float> &fx) {
   put_factor(a.tz[k], fz, a.kb);
   put_factor(a.tx[k], fx, a.kb);
-  march_exps(fz, &a.texp[k][0], &a.tsum[k][0]);
-  march_exps(fx, &a.texp[k][1], &a.tsum[k][1]);
 }
 
 struct RunState {

@@ -85,11 +85,9 @@ struct SepPassArgs {
   const float *nsz[kSepFwdViews];     // backward with normalisation: 1 ⊛ X_v = nsz[z]·nsx[x]
   const float *nsx[kSepFwdViews];     //   (separable; null: no normalisation)
   const float *wpl[kSepFwdViews];     // backward: per-pixel weights (plane sets), or null
-  // wave-per-tile passes (k_march.hip): taps per factor, tiles of the launch, and
-  // for each view's z and x factor the power of two that puts its largest tap
-  // into [2^13, 2^14) and the exponent of a bound on its absolute sum
+  // wave-per-tile passes (k_march.hip): taps per factor, tiles of the launch, waves
+  // of a fused work-group
   int kb, ntiles, waves;
-  int texp[kSepFwdViews][2], tsum[kSepFwdViews][2];
   float tz[kSepFwdViews][kMaxK];      // z factor, padded to the bucket
   float tx[kSepFwdViews][kMaxK];      // x factor, padded to the bucket
 };
