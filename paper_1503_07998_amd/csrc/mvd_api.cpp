@@ -572,7 +572,8 @@ struct Tune {
   int pq_zseg_scale = 0;  // persistent batches: segment length × 2^(v − 2) of the planner's (0: × 2)
   int terms = 1;        // kernels of several rank-one terms: two terms per launch (0: one)
   int fused = 2;        // one launch per update (forward and backward passes together): 0 never, 1 for
-                        // simultaneous two-view runs wherever it applies, 2 where it is the faster form
+                        // simultaneous two-view runs wherever it applies, 2 where it is the faster form,
+                        // 3 (the tuner's) as 1 where the wave tiles' inputs are finite
   int wide = 0;         // rows of 513–1024 columns as one column per thread in up to
                         // 1024-thread work-groups (one-ring passes): 0 where it applies, 2 never
 };
@@ -885,6 +886,7 @@ struct RunState {
   const Tune *tn = &tune();   // launch-shape choices (environment or autotuner)
   bool normalize = false;     // divide back-projections by 1 ⊛ X_v (MVD_FLAG_NORMALIZE)
   int update = MVD_UPDATE_SIMULTANEOUS;
+  bool finite = false;        // whole-number observations and no given ψ^0: nothing is infinite or NaN
   const float *const *wpl = nullptr;   // per-pixel weight planes of the whole volume, or null
   size_t wpl_off = 0;                  // elements from their start to this launch's first plane
   float *acc = nullptr;                // partial sums of low-rank kernels' terms (a plane set), or null
@@ -1770,6 +1772,8 @@ hipError_t fused_iteration(const RunState &st, const ObsRef &ob, int kb, const f
 // updated simultaneously under the zero boundary, rank-one PSFs and
 // back-projectors of 8 to 33 taps, the plain update, rows of whole 16-byte
 // chunks and aligned planes.  Returns the common bucket, or 0.
+// It does not form outputs again that an infinity or NaN beside them spoils (its
+// ratios are on no plane): unless asked for, only where none can come in.
 // The fused form moves 12 (uint16) or 16 bytes per voxel against 32 or 40, but
 // runs fewer waves and more steps per segment: it is the faster form where the
 // two launches' planes do not stay in the 256 MB last-level cache between them, its
@@ -1784,8 +1788,8 @@ hipError_t fused_iteration(const RunState &st, const ObsRef &ob, int kb, const f
 int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const float *est, const float *other,
                        const float *checkpoints) {
   const mvd_ctx *c = st.c;
-  if (st.tn->fused == 0 || c->nv != 2 || update != MVD_UPDATE_SIMULTANEOUS || st.boundary != MVD_BOUNDARY_ZERO ||
-      st.force2d || st.normalize || st.wpl)
+  if (st.tn->fused == 0 || (st.tn->fused != 1 && !st.finite) || c->nv != 2 || update != MVD_UPDATE_SIMULTANEOUS ||
+      st.boundary != MVD_BOUNDARY_ZERO || st.force2d || st.normalize || st.wpl)
     return 0;
   for (int v = 0; v < 2; ++v)
     if (!c->views[v].sep_p || !c->views[v].sep_x || (uintptr_t)ob.p[v] % (ob.u16 ? 8 : 16) != 0) return 0;
@@ -1795,7 +1799,7 @@ int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const f
   const int kb = march_bucket(c, st.boundary, update);
   if (kb == 0 || kb > 33) return 0;
   const double bytes = (double)st.g.Y * st.g.Z * st.g.X * (ob.u16 ? 16 : 20);
-  if (st.tn->fused != 1) {
+  if (st.tn->fused == 2) {
     SepPassArgs a{};
     fused_geom(a, st.g, kb);
     const int steps = (st.g.Z + 31) / 32;
@@ -1843,6 +1847,7 @@ hipError_t enqueue_run(mvd_ctx *c, const void *const *obs, float *est, const mvd
   RunState rs{c,  g, r->boundary, (r->flags & MVD_FLAG_FORCE_2D) != 0, s, r->view_weights,
               timing_override || (r->flags & MVD_FLAG_TIMING) != 0, &tn};
   rs.update = r->update;
+  rs.finite = r->obs_dtype == MVD_U16 && (r->init == MVD_INIT_MEAN || (r->init == MVD_INIT_CONST && std::isfinite(r->init_const)));
   rs.normalize = (r->flags & MVD_FLAG_NORMALIZE) != 0;
   rs.wpl = r->weight_planes;
   if (L.acc) rs.acc = reinterpret_cast<float *>(ws + L.acc_off);
@@ -1895,7 +1900,7 @@ hipError_t enqueue_run(mvd_ctx *c, const void *const *obs, float *est, const mvd
     // (after an odd count ψ^T is copied back to the estimate)
     const int kbf = r->update == MVD_UPDATE_SIMULTANEOUS && L.n_ratio > 0 && aligned16(est_b) &&
                             aligned16(rat[0]) && (!r->checkpoints || aligned16(r->checkpoints)) && !kbm &&
-                            tn.fused == 1
+                            (tn.fused & 1)
                         ? fused_bucket_of(rb, ob)
                         : 0;
     const bool pingpong = kbf && !r->checkpoints && g.X > kFusedStrip;
@@ -2450,7 +2455,7 @@ hipError_t cached_graph(mvd_ctx *c, const void *const *obs, float *est, const mv
 std::vector<Tune> tune_candidates() {
   std::vector<Tune> c(12, tune());
   for (size_t i = 1; i < c.size(); ++i) c[i].fused = 0;
-  c[11].fused = 1;       // one fused launch per iteration (where it applies)
+  c[11].fused = 3;       // one fused launch per iteration (where it applies)
   c[1].fwd_occ = 2;
   c[2].fwd_views = 1;
   c[3].bwd_vin = 1;      // one ratio plane per backward launch
