@@ -193,7 +193,6 @@ struct mvd_ctx {
   size_t d_taps_cap = 0;
   size_t frag_off = 0;             // bytes into d_taps of the Toeplitz operands [V][2][kzm] (kernels that
                                    // need K×K passes of at most 33 columns), or 0
-  std::vector<int> frag_texp;      // their powers of two
   std::string err;
   // launch timing (MVD_FLAG_TIMING)
   struct Mark {
@@ -286,36 +285,36 @@ std::vector<float> to_f32(const std::vector<double> &v) {
 constexpr int kTapSets = 4;
 constexpr int kFragSets = 2;   // of which have Toeplitz operands too: P_v, X_v
 
-// Toeplitz operands (kFragRowBytes per tap row) of a correlation with ft[kz][pitch],
-// kx columns used, as 16-bit pairs of the taps times 2^*texp (the largest in
-// [2^13, 2^14)).
-void fill_frags(const float *ft, int kz, int kx, int pitch, float *out, int *texp) {
-  double m = 0.0;
-  for (int j = 0; j < kz; ++j)
-    for (int q = 0; q < kx; ++q) m = std::max(m, std::fabs((double)ft[(size_t)j * pitch + q]));
-  *texp = m > 0.0 ? std::min(13 - std::ilogb(m), 100) : 0;   // (scales stay normal float32 numbers)
-  // a row's taps in a padded line, so that a lane's four values are neighbours there
-  _Float16 *d = reinterpret_cast<_Float16 *>(out);
-  const int rx = (kx - 1) / 2, pad = 32;
-  std::vector<_Float16> hi(kx + 2 * pad), lo(kx + 2 * pad);
-  const double s = std::ldexp(1.0, *texp);
-  for (int j = 0; j < kz; ++j, d += kFragRowBytes / sizeof(_Float16)) {
-    for (int q = 0; q < kx; ++q) {
-      const float y = (float)(ft[(size_t)j * pitch + q] * s);
-      hi[pad + q] = (_Float16)y;
-      lo[pad + q] = (_Float16)(y - (float)hi[pad + q]);
-    }
-    for (int lane = 0; lane < 64; ++lane)
-      for (int u = 0; u < 3; ++u) {
-        const int q = 16 * (u - 1) + 4 * (lane / 16) - lane % 16 + rx;  
-        const bool in = q + 3 >= 0 && q < kx;
-        _Float16 *at = u < 2 ? d + lane * 8 + 4 * u : d + 1024 + lane * 4;
-        for (int e = 0; e < 4 && in; ++e) {
-          at[e] = hi[pad + q + e];
-          at[(u < 2 ? 512 : 256) + e] = lo[pad + q + e];
-        }
-      }
+// x as the sum of three bfloat16 values, each rounded to nearest even.
+void bf16_parts(float x, uint16_t (&p)[3]) {
+  for (int k = 0; k < 3; ++k) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    u = (u + 0x7fffu + ((u >> 16) & 1)) & 0xffff0000u;
+    p[k] = (uint16_t)(u >> 16);
+    float y;
+    std::memcpy(&y, &u, 4);
+    x -= y;
   }
+}
+
+// Toeplitz operands (kFragRowBytes per tap row) of a correlation with ft[kz][pitch],
+// kx columns used.
+void fill_frags(const float *ft, int kz, int kx, int pitch, float *out) {
+  uint16_t *d = reinterpret_cast<uint16_t *>(out);
+  const int rx = (kx - 1) / 2;
+  for (int j = 0; j < kz; ++j)
+    for (int u = 0; u < 3; ++u, d += 64 * 12)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int e = 0; e < 4; ++e) {
+          const int q = 16 * (u - 1) + 4 * (lane / 16) - lane % 16 + rx + e;
+          if (q < 0 || q >= kx) continue;   // (zeros)
+          uint16_t p[3];
+          bf16_parts(ft[(size_t)j * pitch + q], p);
+          d[lane * 8 + e] = p[2];
+          d[lane * 8 + 4 + e] = p[0];
+          d[512 + lane * 4 + e] = p[1];
+        }
 }
 
 size_t norm_stride(const mvd_ctx *c) { return (size_t)((c->Z + 3) / 4 * 4) + (size_t)((c->X + 3) / 4 * 4); }
@@ -419,10 +418,9 @@ mvd_status derive(mvd_ctx *c) {
           }
       }
     }
-    c->frag_texp.assign((size_t)c->nv * kFragSets, 0);
-    for (size_t set = 0; c->frag_off && set < c->frag_texp.size(); ++set)
-      fill_frags(host.data() + (set / kFragSets * kTapSets + set % kFragSets) * per, c->kzm, c->kxm, c->kxpm, host.data() + frag_at + set * frag_set,
-                 &c->frag_texp[set]);
+    for (size_t set = 0; c->frag_off && set < (size_t)c->nv * kFragSets; ++set)
+      fill_frags(host.data() + (set / kFragSets * kTapSets + set % kFragSets) * per, c->kzm, c->kxm, c->kxpm,
+                 host.data() + frag_at + set * frag_set);
     DeviceGuard dg(c->device);
     if (!dg.ok()) return fail(c, MVD_ERR_DEVICE, "cannot select device %d", c->device);
     const size_t bytes = host.size() * sizeof(float);
@@ -933,7 +931,6 @@ void set_2d_taps(TwoDPassArgs &a, int k, const mvd_ctx *c, int v, int which) {
   a.taps[k] = dtaps(c, v, which);
   const bool frags = c->frag_off && !c->float32 && which < kFragSets;
   a.frag[k] = frags ? reinterpret_cast<const char *>(c->d_taps) + c->frag_off + set * c->kzm * kFragRowBytes : nullptr;
-  a.texp[k] = frags ? c->frag_texp[set] : 0;
 }
 
 // Rows of whole 16-byte chunks in every plane of the pass?

@@ -123,16 +123,15 @@ struct TwoDPassArgs {
   const float *taps[k2dViews];        // device [kz][kx] per view
   int mfma;                            // 1: matrix-core kernels, 0: vector-ALU kernels
   // 16-bit form (k_2d_split.hip): per view the Toeplitz operands of its tap rows
-  // (device; null: not this form) and the power of two in them; vec: rows of whole
-  // 16-byte chunks, every plane aligned, zero boundary
+  // (device; null: not this form); vec: rows of whole 16-byte chunks, every plane
+  // aligned, zero boundary
   const void *frag[k2dViews];
-  int texp[k2dViews];
   int vec;
 };
 // Toeplitz operands of one tap row: for lane (o = lane % 16, g = lane / 16), value
 // 4u + e is the tap of position 16 (u − 1) + 4g + e relative to the output block for
-// output o; [hi, lo][lane] of values 0 … 7, then [hi, lo][lane] of values 8 … 11.
-constexpr size_t kFragRowBytes = 2 * 64 * 24;
+// output o, in three bfloat16 parts a, b, c; per unit u [lane] of c and a, then [lane] of b.
+constexpr size_t kFragRowBytes = 3 * 64 * 24;
 bool split2d_takes(const TwoDPassArgs &a);
 hipError_t launch_2d_split(const TwoDPassArgs &a, bool forward, hipStream_t s);
 
