@@ -444,7 +444,9 @@ mvd_status mvd_backward_grads(mvd_ctx *ctx, const void *const *obs, const float 
  * Items that the persistent kernel does not take (K×K or > 41-tap passes,
  * normalised or per-pixel-weighted updates, checkpoints, rows that are not
  * whole 16-byte units) make the batch a HIP graph instead: every volume's
- * whole iteration loop as one branch.  Results equal mvd_deconvolve_planes
+ * whole iteration loop as one branch.  So does size where the graph is the
+ * faster form: untuned batches of at least 1 Mvoxel with few volumes (their
+ * passes at most 12 times those of the longest) or of 16 Mvoxel.  Results equal mvd_deconvolve_planes
  * bitwise in both forms.  Items are copied; their device buffers must stay
  * valid and unchanged in address while the batch exists. */
 typedef struct {
@@ -463,7 +465,8 @@ typedef struct mvd_batch mvd_batch;
                                form applies too, both forms are built and timed (three whole
                                launches each on `stream`, overwriting the items' estimates) and
                                the faster is kept; not when an item's ψ^0 is given
-                               (MVD_INIT_GIVEN), which keeps the persistent form. */
+                               (MVD_INIT_GIVEN): such a batch takes its form as untuned
+                               ones do. */
 #define MVD_BATCH_GRAPH 0x2u /* use the graph form even where the persistent form applies */
 
 /* Validate every item, optionally autotune, and capture the batch graph.

@@ -175,11 +175,9 @@ __device__ __forceinline__ bool wait_plane(const PqQueue &q, KJob *j, int y, uns
   return true;
 }
 
-// Work-groups of kPqThreads threads.  A job whose tiles need at most half of
-// them runs two tiles per item, one in each half (the tiles of an item share
-// their row segment, so both halves execute the same barriers; a lone tile's
-// partner half executes its barriers only); a wider job runs one tile with
-// every thread.
+// Work-groups of kPqThreads threads.  An item is two tiles, one in each half (they
+// share their row segment, so both halves execute the same barriers; a lone tile's
+// partner half executes its barriers only).
 __global__ void __launch_bounds__(kPqThreads, 2) pq_kernel(PqQueue q) {
   __shared__ int s_item, s_go;
   extern __shared__ __align__(16) float lds_all[];
@@ -204,10 +202,9 @@ __global__ void __launch_bounds__(kPqThreads, 2) pq_kernel(PqQueue q) {
     }
     __syncthreads();
     if (s_go) {
-      const bool pair = j->pair != 0;
-      const int half = pair ? (int)(threadIdx.x / (kPqThreads / 2)) : 0;   // wave-uniform
-      const int t = pair ? (int)(threadIdx.x % (kPqThreads / 2)) : (int)threadIdx.x;
-      const int nt = pair ? kPqThreads / 2 : kPqThreads;
+      const int half = (int)(threadIdx.x / (kPqThreads / 2));   // wave-uniform
+      const int t = (int)(threadIdx.x % (kPqThreads / 2));
+      const int nt = kPqThreads / 2;
       const int b = half ? b1 : b0;
       const uint32_t lds_off = (uint32_t)half * (uint32_t)j->lds_floats;
       if (phase == 0) {

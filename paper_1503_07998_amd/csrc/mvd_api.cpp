@@ -2572,7 +2572,23 @@ hipError_t autotune(mvd_ctx *c, const void *const *obs, float *est, const mvd_ru
 // Whether a run can go through the persistent queue kernel: rank-one passes
 // of at most 41 taps, the plain update (no normalisation, no per-pixel
 // weights), no checkpoints, and whole 16-byte row items.
-constexpr double kPqMostTiled = 8e6;   // voxels on wave tiles beyond which a batch runs as a graph
+// Is an untuned batch of `voxels` in all, `launches` passes in its items' plain runs
+// and `chain` in the longest of them better off as a graph?  A graph's small launches
+// leave one after the other, 3.8 µs each, whatever the number of branches; the queue
+// takes about 50 µs per link of the longest chain for any number of items, and then
+// 0.10 (7 taps) to 0.24 ms (31 taps) per Mvoxel of 40 passes against 0.09 to 0.12.
+// Measured, ms per launch, queue / graph, 10 sequential iterations of two or three
+// float32 views, 21 and 31 taps on wave tiles: 3 volumes, 2.1 Mvoxel 3.1 / 0.7, 8.5
+// Mvoxel 3.4 / 1.2, 34 Mvoxel 10.5 / 4.1; 8 volumes, 2 Mvoxel 2.1 / 1.3; 20 volumes, 1.3
+// Mvoxel 1.5 / 2.8, 4 Mvoxel 2.3 / 3.2, 8.2 Mvoxel 2.5 / 3.2; 40 volumes, 8.2 Mvoxel 2.5 /
+// 5.8.  The float32 passes: 3 volumes, 2.1 Mvoxel 2.9 / 1.0, 34 Mvoxel 7.9 / 4.3; 7 taps
+// 2.3 / 0.8 and 7.7 / 3.5; 20 volumes of 7 taps, 4 Mvoxel 2.2 / 3.1, 20 Mvoxel 4.3 / 3.2.
+// Below 1 Mvoxel making a graph (1 to 8 ms against 0.1 to 0.3 for the queue) costs
+// what one launch saves: 3 volumes, 0.27 Mvoxel, first launch included, 2.6 ms / 2.3.
+bool batch_as_graph(double voxels, long launches, long chain) {
+  constexpr double kSmall = 1e6, kLarge = 16e6;
+  return voxels >= kSmall && (voxels >= kLarge || launches <= 12 * chain);
+}
 
 bool pq_eligible(const mvd_ctx *c, const void *const *obs, const float *est, const mvd_run *r, std::string *why) {
   auto no = [&](const char *m) {
@@ -2844,7 +2860,7 @@ hipError_t pq_setup(mvd_batch *b, int window) {
   q.exited = done + ndone + 1;
   q.giveup = done + ndone + 2;
   size_t lds = 0;
-  for (const PqJob &j : jobs) lds = std::max(lds, (j.pair ? 2 : 1) * (size_t)j.lds_floats * sizeof(float));
+  for (const PqJob &j : jobs) lds = std::max(lds, 2 * (size_t)j.lds_floats * sizeof(float));
   if (lds > kLdsLimit) return hipErrorInvalidValue;
   b->pq.lds = lds;
   int per_cu = 0, cus = 0;
@@ -3663,7 +3679,8 @@ mvd_status mvd_batch_create(mvd_batch **out, const mvd_item *items, int n_items,
   hipError_t e = hipSuccess;
   // the persistent queue form where every item allows it, else the graph form
   bool pq = !(flags & MVD_BATCH_GRAPH);
-  double tiled = 0.0;   // voxels whose passes run on wave tiles
+  double voxels = 0.0;
+  long launches = 0, chain = 0;
   for (size_t i = 0; i < b->items.size() && pq; ++i) {
     const auto &it = b->items[i];
     std::string why;
@@ -3671,20 +3688,19 @@ mvd_status mvd_batch_create(mvd_batch **out, const mvd_item *items, int n_items,
       pq = false;
       b->why_graph = "item " + std::to_string(i) + ": " + why;
     }
-    if (march_bucket(it.ctx, it.run.boundary, it.run.update))
-      tiled += (double)it.run.n_planes * it.ctx->Z * it.ctx->X;
+    voxels += (double)it.run.n_planes * it.ctx->Z * it.ctx->X;
+    const int V = it.ctx->nv;
+    const long n = (long)it.run.n_iters * 2 * (it.run.update == MVD_UPDATE_SIMULTANEOUS ? (V + 1) / 2 : V);
+    launches += n;
+    chain = std::max(chain, n);
   }
   // with MVD_BATCH_TUNE both forms are built and timed (unless an item's given
   // ψ^0 would be overwritten by the timing launches)
   bool both = (flags & MVD_BATCH_TUNE) != 0;
   for (const auto &it : b->items) both = both && it.run.init != MVD_INIT_GIVEN;
-  // The queue's work-groups hold two waves per SIMD, the wave tiles' own launches
-  // three.  Three volumes, 10 sequential iterations, ms, the queue with wave tiles / with
-  // the float32 tiles before / the graph: 1.6 Mvoxel 3.3 / 4.1 / 0.7, 6.6 Mvoxel 3.8 /
-  // 4.3 / 1.0, 26 Mvoxel 11.4 / 7.5 / 3.1, 288 Mvoxel 101 / 65 / 58.
-  if (pq && !both && tiled >= kPqMostTiled) {
+  if (pq && !both && batch_as_graph(voxels, launches, chain)) {
     pq = false;
-    b->why_graph = "large volumes on wave tiles";
+    b->why_graph = "the graph form is faster for volumes of this size";
   }
   if (pq) {
     e = pq_setup(b, tune().pq_window);

@@ -310,7 +310,7 @@ struct PqJob {
   PlaneGeom g;
   int kb;                      // kernel-size bucket of every pass
   int march;                   // 1: wave-per-tile passes (k_march_impl.hpp), a tile being kPqHalfWaves strips
-  int pair;                    // 1: tiles of ≤ kPqThreads/2 threads, two per item; 0: one tile per item
+  int pair;                    // two tiles per item (0, one, only in the order's host test)
   int lds_floats;              // LDS of one tile (floats; the second tile of a pair starts there)
   int nseg, nstrip, zseg, x_out, ntiles;   // tiling (ntiles = nseg · nstrip per plane)
   int sim, nf, per_iter;
