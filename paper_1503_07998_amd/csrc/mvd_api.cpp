@@ -750,20 +750,33 @@ void put_factor(float *dst, const std::vector<float> &f, int kb) {
 constexpr int kMarchMinTaps = 8;
 
 // Are the float32 passes the better ones for kernels of k taps in planes X wide?
-// Both families are near the memory's rate on large volumes; the float32 passes
-// read whole rows per work-group, which the memory prefers where a row fills the
-// work-group's power of two of threads.  `alone`: one input plane set per launch
-// (sequential updates, single views).  Measured, µs per run of 10 iterations,
-// uint16, wave tiles / float32: alone, 11 taps, 122 planes of 512×512 3212 / 2861
-// and 217 of 384×384 2800 / 3279 (rows that do not fill their work-group); alone,
-// 21 taps, 488 of 256×256 3209 / 2794, but 31 taps, 64 of 512×512 1438 / 1619; two
-// views together, 41 taps, 256 of 512×512 7401 / 6383, but 21 taps 3821 / 4905; two
-// together, 15 taps, 1953 of 128×128 2427 / 2294, but 61 of them 222 / 257, and
-// planes so small seldom come by the thousand.
-// Two together with more than 33 taps (a launch each on the wave tiles): 248 planes
-// of 171×87 1293 / 1102, 40 of 300×445 1630 / 1390, but 20 of 300×1030 1469 / 2762.
+// They read whole rows per work-group and their matrix work grows with the taps; the
+// wave tiles' is the same for 8 to 33 taps, and a launch of few planes spreads over
+// more of the chip.  So the float32 passes win with short kernels on large volumes.
 // The choice depends on nothing that changes between a run over some planes of a
-// volume and one over all, so that their results stay equal.
+// volume and one over all, so that their results stay equal: planes of at least 2¹⁶
+// pixels are taken as parts of large volumes, smaller ones as parts of small ones.
+// `alone`: one input plane set per launch (sequential updates, single views).
+// Measured, µs per run of 10 iterations, two views of uint16, wave tiles / float32:
+//   together, 9 and 15 taps: 64 planes of 512×512 1427 / 1007 and 1408 / 1127, 256 of
+//     256×256 1186 / 1000 and 1169 / 1060, 64 of 512×640 1938 / 1728 and 1932 / 1808 (but 8 of
+//     512×512 at 15 329 / 326, 4 of 256×256 205 / 232); 32 of 128×256 218 / 234 and 217 / 247;
+//     rows below 256: 32 of 256×128 221 / 222 and 218 / 241, 30 of 136×128 225 / 275 at 15,
+//     32 of 128×128 208 / 212 and 207 / 224, 200 of 256×128 629 / 593 and 627 / 636, 1000 of
+//     128×128 1306 / 1129 and 1306 / 1178;
+//   together, 21 taps: 256 planes of 512×512 4787 / 4958, 200 of 384×384 2715 / 2756; 31 taps:
+//     128 of 512×512 2451 / 2978; 41 taps (a launch each on the wave tiles): 256 of
+//     512×512 8540 / 6482, 248 of 171×87 1346 / 1089, 40 of 300×445 1692 / 1350, but 20 of
+//     300×1030 1526 / 2721 (strips with halo columns there);
+//   alone, 9 and 15 taps: 64 planes of 512×512 1670 / 1278 and 1669 / 1309, 64 of 512×640
+//     1983 / 1687 and 1986 / 1675, 1000 of 128×128 1584 / 1311 and 1583 / 1381 (32 of them
+//     290 / 346);
+//   alone, 21 taps: 128 planes of 512×512 3500 / 2949, 256 of 256×256 1612 / 1516, but 200 of
+//     384×384 3118 / 3638 (rows that leave an eighth of their power-of-two work-group
+//     idle), 16 of 1024×1024 1625 / 1688, 1000 of 128×128 1579 / 1545, 128 of them 411 / 505;
+//   alone, 31 taps: 64 of 512×512 1695 / 1654, 256 of 256×256 1598 / 1668, 100 of 512×768
+//     4474 / 4896; 41 taps: 256 of 256×256 2029 / 1881, 64 of 512×512 2100 / 1860, 64 of
+//     1000×1000 (float32) 8027 / 8032.
 // Under the periodic boundary always (the tiles' chunks would cross the planes'
 // edges; read by elements they took 3867 µs against 1719, 64 planes of 512×512, two
 // views, 11 taps).
@@ -771,12 +784,12 @@ bool float32_better(int Z, int X, int boundary, int k, bool alone) {
   if (boundary != MVD_BOUNDARY_ZERO) return true;
   int p2 = 1;
   while (p2 < X) p2 *= 2;
-  if (k > 33 && !alone) return X <= 1024;
-  if (X % 8 || X > 1024 || 8 * X < 7 * p2) return false;
-  if (k <= 15) return alone || (X < 256 && (long)Z * X > 128 * 128);
-  if (k <= 21) return alone;
-  if (k <= 33) return false;
-  return X <= 256;
+  const bool fills = X % 8 == 0 && 8 * X >= 7 * p2;
+  if (k > 33) return alone ? fills && X <= 512 : X <= 1024;
+  if (X % 8 || X > 1024 || k > 21) return false;
+  const bool large = X >= 256 && (long)Z * X >= 1L << 16;
+  if (k <= 15) return large || (alone && fills);
+  return alone && fills && X >= 256 && X <= 512;
 }
 
 // The bucket of every rank-one pass of a context's runs with this update (one
@@ -1771,17 +1784,16 @@ hipError_t fused_iteration(const RunState &st, const ObsRef &ob, int kb, const f
 // chunks and aligned planes.  Returns the common bucket, or 0.
 // It does not form outputs again that an infinity or NaN beside them spoils (its
 // ratios are on no plane): unless asked for, only where none can come in.
-// The fused form moves 12 (uint16) or 16 bytes per voxel against 32 or 40, but
-// runs fewer waves and more steps per segment: it is the faster form where the
-// two launches' planes do not stay in the 256 MB last-level cache between them, its
-// strips take whole work-groups (rows of 64, 128 or 384 columns do not: 8369, 3290
-// and 2821 µs per 10 iterations for 32 Mvoxel of uint16 where 256, 512 and 1024 take
-// 1930) and the launch's last round of work-groups is not mostly empty.  Measured at
-// 31 taps, planes of 512×512, two launches against fused, µs per iteration: uint16
-// 71.9 / 77.5 at 32 planes (134 MB in two launches), 112.5 / 112.1 at 64 (268 MB),
-// 201.8 / 184.7 at 96 (65 % of the rounds' slots busy), 247.2 / 190.2 at 128 (87 %);
-// float32 128.4 / 126.4 at 64 (335 MB), 189.7 / 208.7 at 96, 254.4 / 217.0 at 128
-// (671 MB).
+// The fused form moves 12 bytes per voxel of uint16 against 32, but runs fewer waves
+// and more steps per segment: it is the faster form where the two launches' planes do
+// not stay in the 256 MB last-level cache between them, its strips take whole
+// work-groups (rows of 64, 128 or 384 columns do not) and the launch's last round of
+// work-groups is not mostly empty.  Measured, 31 taps, µs per 10 iterations, two
+// launches / fused, uint16: 64 planes of 512×512 (268 MB in two launches) 1257 / 1396, 96
+// (402 MB) 2407 / 2341, 128 (537 MB) 2757 / 2452, 512 10317 / 9594; 24 of 1024×1024 (402 MB)
+// 2403 / 2480, 64 5394 / 4732; 4 of 2048×2048 1256 / 1445, 16 5520 / 4864.  Float32
+// observations: 128 planes of 512×512 2835 / 2877, 512 10735 / 11236, 16 of 2048×2048 5625 /
+// 5637: never.
 int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const float *est, const float *other,
                        const float *checkpoints) {
   const mvd_ctx *c = st.c;
@@ -1795,14 +1807,13 @@ int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const f
     return 0;
   const int kb = march_bucket(c, st.boundary, update);
   if (kb == 0 || kb > 33) return 0;
-  const double bytes = (double)st.g.Y * st.g.Z * st.g.X * (ob.u16 ? 16 : 20);
+  const double bytes = (double)st.g.Y * st.g.Z * st.g.X * 16;   // ψ, φ_v and r_v
   if (st.tn->fused == 2) {
     SepPassArgs a{};
     fused_geom(a, st.g, kb);
     const int steps = (st.g.Z + 31) / 32;
     const double rounds = (a.ntiles + 255) / 256, busy = (double)st.g.Y * a.nstrip * steps / (256 * rounds * (a.zseg / 32 + 2.5));
-    if (bytes < (ob.u16 ? 256e6 : 640e6) || (st.g.X + 31) / 32 % kMarchFusedWaves || busy < (ob.u16 ? 0.62 : 0.7))
-      return 0;
+    if (bytes < 480e6 || (st.g.X + 31) / 32 % kMarchFusedWaves || busy < 0.62) return 0;
   }
   return kb;
 }
