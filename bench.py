@@ -29,6 +29,7 @@ HBM_PEAK = 8.0e12            # B/s, MI355X HBM3E
 # 2 flop × 2.4 GHz (the library is built with packed FP32 disabled)
 ALU_PEAK = 256 * 4 * 16 * 2 * 2.4e9
 MFMA_F32_PEAK = 157.3e12     # dense FP32 matrix-core peak (the general K×K passes)
+MFMA_BF16_PEAK = 2.5e15      # dense bf16 matrix-core peak (the wave tiles)
 
 
 def log(msg):
@@ -123,20 +124,50 @@ def kernel_code_hash(*paths):
 
 
 # the sources of the pass kernels whose counters the traffic record holds: the
-# separable passes, and the fused iteration (which also includes the former)
-PASS_SOURCES = {"sep": ("k_sep_impl.hpp",), "fused": ("k_sep_impl.hpp", "k_fused.hip")}
+# float32 separable passes, their fused iteration (which also includes the former),
+# and the wave tiles (both forms)
+PASS_SOURCES = {"sep": ("k_sep_impl.hpp",), "fused": ("k_sep_impl.hpp", "k_fused.hip"),
+                "tiles": ("k_march_impl.hpp", "k_march_launch.hpp", "k_march.hip")}
 
 
 def pass_code_hash(family="sep"):
     return kernel_code_hash(*[os.path.join(ROOT, "paper_1503_07998_amd", "csrc", f) for f in PASS_SOURCES[family]])
 
 
-def measured_traffic(name, kind):
+def pass_family(kind, tiles):
+    return "tiles" if tiles else "fused" if kind == "fused" else "sep"
+
+
+def kernel_family(kernel):
+    """Family of a kernel by its name in a trace, or None (not a pass)."""
+    if "march::" in kernel:
+        return "tiles"
+    if "fused_kernel" in kernel:
+        return "fused"
+    return "sep" if "sep_forward" in kernel or "sep_backward" in kernel else None
+
+
+def wave_tiles(ctx, spec):
+    """Do this context's passes of ``spec`` run on the library's wave tiles?"""
+    import ctypes
+
+    from paper_1503_07998_amd import _native as N
+
+    f = N.lib().mvd_internal_wave_tiles
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    r = f(ctx, N.BOUNDARY[spec.boundary], N.UPDATE[spec.update])
+    if r < 0:
+        raise N.MvdError(r, "mvd_internal_wave_tiles")
+    return bool(r)
+
+
+def measured_traffic(name, kind, tiles=False):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE runs (scaled by the factors a copy of known size
     gives), or None when the kernel code changed since they were taken."""
     path = os.path.join(ROOT, "profiles", f"sep_passes_{name}_traffic.json")
-    family = "fused" if kind == "fused" else "sep"
+    family = pass_family(kind, tiles)
     try:
         rec = json.load(open(path))
         h = pass_code_hash(family)
@@ -146,8 +177,10 @@ def measured_traffic(name, kind):
         return None
     # the instance of the pass (plain, split-view or fused form) that ran most
     # often in the profiled bench run
-    names = ("fused_kernel",) if kind == "fused" else (f"sep_{kind}_kernel", f"sep_{kind}_split_kernel")
-    cands = [(k, v) for k, v in rec["kernels"].items() if any(n in k for n in names)]
+    names = ("fused_kernel",) if kind == "fused" else (
+        (f"::{kind}_kernel",) if tiles else (f"sep_{kind}_kernel", f"sep_{kind}_split_kernel"))
+    cands = [(k, v) for k, v in rec["kernels"].items()
+             if kernel_family(k) == family and any(n in k for n in names)]
     if not cands:
         return None
     k, v = max(cands, key=lambda kv: kv[1].get("trace_calls", 0))
@@ -185,7 +218,7 @@ def copy_rate_gbs(nbytes=1 << 30, reps=5):
     return 2 * nbytes / (ms / 1e3) / 1e9
 
 
-def roofline(spec, kinds, general=False, variant=False):
+def roofline(spec, kinds, general=False, variant=False, tiles=False):
     """Roofline entry of the kernel with the largest share of the step.
 
     ``variant`` marks a run whose passes are other kernel instances than the
@@ -195,12 +228,13 @@ def roofline(spec, kinds, general=False, variant=False):
     The binding ceiling is the largest of the HBM time (algorithmic bytes at
     8 TB/s), the vector-ALU time (row-pass flops at 78.6 TFLOP/s) and the
     matrix-core time (column-pass or K×K flops at the 157.3 TFLOP/s FP32
-    matrix peak); `achieved` is measured against that ceiling's peak."""
+    matrix peak; ``tiles``: six bf16 partial products each at the 2.5 PFLOP/s
+    dense bf16 peak); `achieved` is measured against that ceiling's peak."""
     dom = max(kinds, key=lambda k: kinds[k]["avg_ms"] * kinds[k]["launches"])
     kd = kinds[dom]
     sec = kd["avg_ms"] / 1e3
     times = {"hbm": kd["bytes"] / HBM_PEAK, "alu": kd["flops_valu"] / ALU_PEAK,
-             "mfma": kd["flops_mfma"] / MFMA_F32_PEAK}
+             "mfma": kd["flops_mfma"] * (6 if tiles else 1) / (MFMA_BF16_PEAK if tiles else MFMA_F32_PEAK)}
     bound = max(times, key=times.get)
     if bound == "hbm":
         roof = {"bound": "hbm", "achieved": kd["bytes"] / sec / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s"}
@@ -209,15 +243,17 @@ def roofline(spec, kinds, general=False, variant=False):
                 "unit": "TFLOP/s"}
     else:
         # useful flops only: banded Toeplitz operands also multiply zeros
-        roof = {"bound": "mfma", "achieved": kd["flops_mfma"] / sec / 1e12, "peak": MFMA_F32_PEAK / 1e12,
-                "unit": "TFLOP/s"}
+        roof = {"bound": "mfma", "achieved": kd["flops_mfma"] * (6 if tiles else 1) / sec / 1e12,
+                "peak": (MFMA_BF16_PEAK if tiles else MFMA_F32_PEAK) / 1e12, "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    meas = None if general or variant else measured_traffic(spec.name, dom)
+    meas = None if general or variant else measured_traffic(spec.name, dom, tiles)
     roof["traffic"] = meas["bytes"] if meas else None
     if general:
         roof["kernel"] = f"{dom} pass (twod_{dom}_kernel, general {spec.psf_k}x{spec.psf_k})"
     elif meas:
         roof["kernel"] = f"{dom} pass ({meas['instance']})"
+    elif tiles:
+        roof["kernel"] = f"{dom} pass (march::{dom}_kernel, wave tiles, K={spec.psf_k})"
     elif dom == "fused":
         roof["kernel"] = f"fused iteration (fused_kernel, K={spec.psf_k})"
     else:
@@ -414,7 +450,8 @@ def mix_record(args, cpu=True):
     b.close()
     # the dominant kernel of the mix: the (volume, pass) with the largest total launch time
     spec_d, kinds_d = max(per_vol, key=lambda sk: max(k["avg_ms"] * k["launches"] for k in sk[1].values()))
-    roof = roofline(spec_d, kinds_d, variant=True)
+    ctx_d = next(st["dec"].ctx for sp, st in zip(specs, setups) if sp is spec_d)
+    roof = roofline(spec_d, kinds_d, variant=True, tiles=wave_tiles(ctx_d, spec_d))
     roof["kernel"] = f"{spec_d.name}: " + roof["kernel"]
     out = {
         "value": vox_it / (batch_ms / 1e3), "unit": "voxel-iterations/s", "ms_per_step": batch_ms,
@@ -642,7 +679,7 @@ def bench_stream(args, spec):
         "device_resident_value": vox_it / (ms_res / 1e3),
         "device_resident_ms": ms_res,
         "kernels": kinds,
-        "roofline": roofline(spec, kinds),
+        "roofline": roofline(spec, kinds, tiles=wave_tiles(d.ctx, spec)),
     }
     if not args.no_cpu_baseline:
         log("cpu baseline (oracle)")
@@ -850,7 +887,7 @@ def bench_vol2048(args, spec):
             "psf": spec.psf_k, "update": spec.update, "parallelism": "single GPU",
         },
         "kernels": kinds,
-        "roofline": roofline(spec, kinds),
+        "roofline": roofline(spec, kinds, tiles=wave_tiles(d.ctx, spec)),
         "paper_context": PAPER_CONTEXT.get(spec.name),
     }
     del ws, runs
@@ -1045,7 +1082,8 @@ def main():
 
     kinds = launch_kinds(spec, tim, args.steps, Y * Z * X, general=args.force_2d)
     roof = roofline(spec, kinds, general=args.force_2d,
-                    variant=args.normalize or args.pixel_weights or args.psf != "gauss")
+                    variant=args.normalize or args.pixel_weights or args.psf != "gauss",
+                    tiles=not args.force_2d and args.psf == "gauss" and wave_tiles(d.ctx, spec))
     if roof.get("unit") == "GB/s":
         # context beside the peak: what a plain copy kernel streams on this device, measured now
         cr = copy_rate_gbs()

@@ -74,7 +74,14 @@ def main():
     fetch_factor = cal_bytes / (cf[ck[0]] * kib)
     write_factor = cal_bytes / (cw[ck[0]] * kib)
     fetch, write, trace = per_kernel(a.fetch, "FETCH_SIZE"), per_kernel(a.write, "WRITE_SIZE"), trace_stats(a.trace)
+    path = os.path.join(ROOT, "profiles", f"sep_passes_{a.workload}_traffic.json")
+    hashes = {f: bench.pass_code_hash(f) for f in bench.PASS_SOURCES}
+    # entries of kernels that did not run stay while their sources are the same
     kernels = {}
+    if os.path.exists(path):
+        old = json.load(open(path))
+        kernels = {k: v for k, v in old["kernels"].items()
+                   if (f := bench.kernel_family(k)) and old["code_sha256"].get(f) == hashes[f]}
     for k in fetch:
         if k not in write:
             continue
@@ -97,7 +104,7 @@ def main():
         copy_check = {"kernel": pc[0], "read_ratio": cf[pc[0]] * kib * fetch_factor / cal_bytes,
                       "write_ratio": cw[pc[0]] * kib * write_factor / cal_bytes}
     rec = {
-        "code_sha256": {f: bench.pass_code_hash(f) for f in bench.PASS_SOURCES},
+        "code_sha256": hashes,
         "calibration": {"kernel": ck[0], "bytes_read": cal_bytes, "bytes_written": cal_bytes,
                         "fetch_kib": cf[ck[0]], "write_kib": cw[ck[0]]},
         "fetch_factor": fetch_factor, "write_factor": write_factor,
@@ -106,7 +113,6 @@ def main():
         "kernels": kernels,
         "commands": a.command,
     }
-    path = os.path.join(ROOT, "profiles", f"sep_passes_{a.workload}_traffic.json")
     with open(path, "w") as fh:
         json.dump(rec, fh, indent=1)
     print(f"wrote {path}")

@@ -46,6 +46,10 @@ int mvd_internal_split_plan(const mvd_ctx *ctx, int n_planes, int k, int *out);
  * where the bucket has no fused form. */
 int mvd_internal_fused_plan(const mvd_ctx *ctx, int kb, int *out);
 
+/* Do the rank-one passes of ctx's runs under `boundary` and `update` (mvd_update) run
+ * on wave tiles (1) or as float32 passes (0)?  Negative: a status code. */
+int mvd_internal_wave_tiles(const mvd_ctx *ctx, int boundary, int update);
+
 /* The matrix-core K×K pass for a kz × kx kernel.  out[3]: column steps, input
  * tile row pitch, LDS bytes. */
 int mvd_internal_mfma_plan(int kz, int kx, int *out);

@@ -3317,6 +3317,11 @@ int mvd_internal_mfma_plan(int kz, int kx, int *out) {
 
 int mvd_internal_version(void) { return MVD_TESTING_VERSION; }
 
+int mvd_internal_wave_tiles(const mvd_ctx *c, int boundary, int update) {
+  if (!c) return MVD_ERR_ARG;
+  return march_bucket(c, boundary, update) ? 1 : 0;
+}
+
 int mvd_internal_fused_plan(const mvd_ctx *c, int kb, int *out) {
   if (!c || !out) return MVD_ERR_ARG;
   if (kb != 3 && kb != 7 && kb != 11 && kb != 15 && kb != 21 && kb != 31) return MVD_ERR_UNSUPPORTED;
