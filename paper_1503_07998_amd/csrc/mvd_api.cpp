@@ -1789,11 +1789,10 @@ hipError_t fused_iteration(const RunState &st, const ObsRef &ob, int kb, const f
 // not stay in the 256 MB last-level cache between them, its strips take whole
 // work-groups (rows of 64, 128 or 384 columns do not) and the launch's last round of
 // work-groups is not mostly empty.  Measured, 31 taps, µs per 10 iterations, two
-// launches / fused, uint16: 64 planes of 512×512 (268 MB in two launches) 1257 / 1396, 96
-// (402 MB) 2407 / 2341, 128 (537 MB) 2757 / 2452, 512 10317 / 9594; 24 of 1024×1024 (402 MB)
-// 2403 / 2480, 64 5394 / 4732; 4 of 2048×2048 1256 / 1445, 16 5520 / 4864.  Float32
-// observations: 128 planes of 512×512 2835 / 2877, 512 10735 / 11236, 16 of 2048×2048 5625 /
-// 5637: never.
+// launches / fused, uint16: 64 planes of 512×512 (268 MB in two launches) 1254 / 1244, 96
+// (402 MB) 2405 / 2047, 128 2760 / 2172, 512 10550 / 8680; 24 of 1024×1024 (402 MB) 2372 /
+// 2165, 64 5377 / 4247; 4 of 2048×2048 (268 MB) 1220 / 1276, 16 5428 / 4379; 400 of 256×256
+// (60 % of the rounds' slots busy) 2501 / 2023.
 int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const float *est, const float *other,
                        const float *checkpoints) {
   const mvd_ctx *c = st.c;
@@ -1813,7 +1812,7 @@ int march_fused_bucket(const RunState &st, const ObsRef &ob, int update, const f
     fused_geom(a, st.g, kb);
     const int steps = (st.g.Z + 31) / 32;
     const double rounds = (a.ntiles + 255) / 256, busy = (double)st.g.Y * a.nstrip * steps / (256 * rounds * (a.zseg / 32 + 2.5));
-    if (bytes < 480e6 || (st.g.X + 31) / 32 % kMarchFusedWaves || busy < 0.62) return 0;
+    if (bytes < 400e6 || (st.g.X + 31) / 32 % kMarchFusedWaves || busy < 0.58) return 0;
   }
   return kb;
 }
