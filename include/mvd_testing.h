@@ -50,6 +50,13 @@ int mvd_internal_fused_plan(const mvd_ctx *ctx, int kb, int *out);
  * on wave tiles (1) or as float32 passes (0)?  Negative: a status code. */
 int mvd_internal_wave_tiles(const mvd_ctx *ctx, int boundary, int update);
 
+/* Tiling of a wave-tile pass over n_planes planes of ctx's size with kernels of at
+ * most k taps and n_views views per launch, or (fused != 0) of an iteration of two
+ * views in one launch.  out[7]: kernel bucket, row-segment length, segments, column
+ * strips, pairs of 16-column blocks per strip, tiles, LDS bytes per work-group.
+ * MVD_ERR_UNSUPPORTED where there is no such form. */
+int mvd_internal_march_plan(const mvd_ctx *ctx, int n_planes, int k, int n_views, int fused, long *out);
+
 /* The matrix-core K×K pass for a kz × kx kernel.  out[3]: column steps, input
  * tile row pitch, LDS bytes. */
 int mvd_internal_mfma_plan(int kz, int kx, int *out);

@@ -3316,6 +3316,25 @@ int mvd_internal_mfma_plan(int kz, int kx, int *out) {
 
 int mvd_internal_version(void) { return MVD_TESTING_VERSION; }
 
+int mvd_internal_march_plan(const mvd_ctx *c, int n_planes, int k, int n_views, int fused, long *out) {
+  if (!c || !out || n_planes < 1 || k < 1 || n_views < 1 || n_views > kSepFwdViews) return MVD_ERR_ARG;
+  const int kb = sep_bucket(k);
+  if (kb < 0 || (kb > 33 && (fused || n_views > 1))) return MVD_ERR_UNSUPPORTED;
+  SepPassArgs a{};
+  const PlaneGeom g{n_planes, c->Z, c->X};
+  if (fused) {
+    fused_geom(a, g, kb);
+  } else {
+    march_common(a, g, MVD_BOUNDARY_ZERO, kb, n_views);
+    march_tiles(a, march_waves(kb, n_views, false));
+    a.waves = 1;
+  }
+  const long v[7] = {kb, a.zseg, a.nseg, a.nstrip, a.waves, a.ntiles,
+                     (long)march_lds_bytes(kb, fused ? 2 : n_views, fused ? a.waves : 0)};
+  for (int i = 0; i < 7; ++i) out[i] = v[i];
+  return MVD_OK;
+}
+
 int mvd_internal_wave_tiles(const mvd_ctx *c, int boundary, int update) {
   if (!c) return MVD_ERR_ARG;
   return march_bucket(c, boundary, update) ? 1 : 0;

@@ -192,6 +192,7 @@ hipError_t launch_march_forward(const SepPassArgs &a, hipStream_t s);
 hipError_t launch_march_backward(const SepPassArgs &a, hipStream_t s);
 hipError_t launch_march_fused(const MarchFusedArgs &a, hipStream_t s);
 hipError_t launch_march_single(const SepPassArgs &a, int ep, hipStream_t s);   // ep: kEpStore …
+size_t march_lds_bytes(int kb, int nviews, int fused_waves);   // of a work-group (fused_waves 0: a plain pass)
 constexpr int kMarchThreads = 256;     // four waves, a tile each
 constexpr int kMarchFusedWaves = 8;    // fused form: at most this many, a strip together
 // Waves per SIMD of a pass (register budget); `more`: access or epilogue forms
