@@ -810,9 +810,9 @@ int march_bucket(const mvd_ctx *c, int boundary, int update) {
 // kernels, the reverse sweep), or 0 for the float32 passes.  Those run two terms
 // per launch where a row is one column per thread of a work-group, the wave
 // tiles up to 33 taps at any width.  Two terms each, µs per run of 10 iterations,
-// wave tiles / float32: 64 planes of 512×512 1928 at 8 to 31 taps / 1633 at 11, 1755
-// at 15, 2000 at 21, 2402 at 31, and 4429 / 2837 at 41; 24 of 512×640 1020 / 2243 at
-// 11, 2621 / 3920 at 41.
+// wave tiles / float32: 64 planes of 512×512 2035 at 8 to 31 taps / 1655 at 11, 1812
+// at 15, 2082 at 21, 2527 at 31, and 4382 / 2925 at 41; 24 of 512×640 1085 / 2237 at
+// 11, 2545 / 3921 at 41.
 int march_single_bucket(const mvd_ctx *c, int boundary, int k) {
   if (c->float32 || k < kMarchMinTaps || boundary != MVD_BOUNDARY_ZERO) return 0;
   if (c->X % 8 == 0 && c->X <= 512 && (k <= 15 || k > 33)) return 0;
@@ -823,7 +823,7 @@ int march_single_bucket(const mvd_ctx *c, int boundary, int k) {
 // run on `units`, up to `waves` of them at a time on a unit, a segment costing
 // `extra` steps beyond its own (its first fragments, the start).  A tile beside
 // another takes about 0.6 of the time of one alone: with that the cost orders the
-// measured times (µs per run of 10 iterations, 21 taps) of 16 planes of 512×512,
+// times measured on operands of two float16 parts (µs per run of 10 iterations, 21 taps) of 16 planes of 512×512,
 // two views, in 4 / 8 / 16 segments (435, 415, 489) and of 64 planes in 1 / 2 / 3 /
 // 4 (1241, 1111, 1425, 1168).
 int march_segments(long strips, int steps, long units, int waves, double extra) {
