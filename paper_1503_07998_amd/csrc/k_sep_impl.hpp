@@ -176,6 +176,30 @@ __device__ __forceinline__ void zero_pads(float *lds, int nrows, KArg *a, int t,
   }
 }
 
+// Zero the 3 LDS columns past the last one that a strip with halo columns stores.
+// The row pass forms 4 outputs from the K + 3 inputs of all of them, so the last
+// block of a strip whose width is no multiple of 4 meets up to 3 columns past
+// its last input there, with zero taps: without this they hold what an earlier
+// work-group left, and zero times an infinity or a NaN is NaN.  (The pitch has
+// room: it is at least the widest strip rounded up to 8, plus K + 3.)
+template <int R>
+__device__ __forceinline__ void zero_tail(float *lds, int nrows, KArg *a, int xout, int t, int nt) {
+  for (int e = t; e < nrows * 3; e += nt) {
+    const int row = e / 3;
+    lds[row * a->ldsw + xout + 2 * R + (e - 3 * row)] = 0.f;
+  }
+}
+
+// LDS columns that only meet zero taps, before the first column pass.  128-bit
+// items (VM 1) are whole, so their strips have no tail.
+template <int R, int VM>
+__device__ __forceinline__ void zero_unused(float *lds, int nrows, KArg *a, int xout, int t, int nt) {
+  if (a->halo == 0)
+    zero_pads<R>(lds, nrows, a, t, nt);
+  else if (VM != 1 && xout % 4 != 0)
+    zero_tail<R>(lds, nrows, a, xout, t, nt);
+}
+
 // A row of zeros standing in for the rows outside the plane under the zero
 // boundary (zero-initialised device memory, never written).
 __device__ float kZeroRow[kMaxPlaneX];
@@ -664,7 +688,7 @@ __device__ __forceinline__ void fwd_tile(KArg *a, int b, int t, int nt, float *l
   constexpr int R = S::R, M = S::M, U = S::U;
   const Geo o = tile_geo(a, b);
   const Cols<C, R> cl(a, o, t, nt);
-  if (a->halo == 0) zero_pads<R>(lds, 2 * NV * G, a, t, nt);
+  zero_unused<R, VM>(lds, 2 * NV * G, a, o.xout, t, nt);
   const int nxb = (o.xout + NX - 1) / NX;
   float *tt = lds + 2 * NV * G * a->ldsw;
   fill_tap_table<KB>(tt, a, NV, t, nt);
@@ -781,7 +805,7 @@ __device__ __forceinline__ void bwd_tile(KArg *a, int b, int t, int nt, float *l
   constexpr int R = S::R, M = S::M, U = S::U;
   const Geo o = tile_geo(a, b);
   const Cols<C, R> cl(a, o, t, nt);
-  if (a->halo == 0) zero_pads<R>(lds, 2 * VIN * G, a, t, nt);
+  zero_unused<R, VM>(lds, 2 * VIN * G, a, o.xout, t, nt);
   const int nxb = (o.xout + NX - 1) / NX;
   float *tt = lds + 2 * VIN * G * a->ldsw;
   fill_tap_table<KB>(tt, a, VIN, t, nt);
