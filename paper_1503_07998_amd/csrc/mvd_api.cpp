@@ -752,43 +752,41 @@ constexpr int kMarchMinTaps = 8;
 // Are the float32 passes the better ones for kernels of k taps in planes X wide?
 // They read whole rows per work-group and their matrix work grows with the taps; the
 // wave tiles' is the same for 8 to 33 taps, and a launch of few planes spreads over
-// more of the chip.  So the float32 passes win with short kernels on large volumes.
-// The choice depends on nothing that changes between a run over some planes of a
-// volume and one over all, so that their results stay equal: planes of at least 2¹⁶
-// pixels are taken as parts of large volumes, smaller ones as parts of small ones.
-// `alone`: one input plane set per launch (sequential updates, single views).
-// Measured, µs per run of 10 iterations, two views of uint16, wave tiles / float32:
-//   together, 9 and 15 taps: 64 planes of 512×512 1427 / 1007 and 1408 / 1127, 256 of
-//     256×256 1186 / 1000 and 1169 / 1060, 64 of 512×640 1938 / 1728 and 1932 / 1808 (but 8 of
-//     512×512 at 15 329 / 326, 4 of 256×256 205 / 232); 32 of 128×256 218 / 234 and 217 / 247;
-//     rows below 256: 32 of 256×128 221 / 222 and 218 / 241, 30 of 136×128 225 / 275 at 15,
-//     32 of 128×128 208 / 212 and 207 / 224, 200 of 256×128 629 / 593 and 627 / 636, 1000 of
-//     128×128 1306 / 1129 and 1306 / 1178;
-//   together, 21 taps: 256 planes of 512×512 4787 / 4958, 200 of 384×384 2715 / 2756; 31 taps:
-//     128 of 512×512 2451 / 2978; 41 taps (a launch each on the wave tiles): 256 of
-//     512×512 8540 / 6482, 248 of 171×87 1346 / 1089, 40 of 300×445 1692 / 1350, but 20 of
-//     300×1030 1526 / 2721 (strips with halo columns there);
-//   alone, 9 and 15 taps: 64 planes of 512×512 1670 / 1278 and 1669 / 1309, 64 of 512×640
-//     1983 / 1687 and 1986 / 1675, 1000 of 128×128 1584 / 1311 and 1583 / 1381 (32 of them
-//     290 / 346);
+// more of the chip.  So short kernels on many planes are the float32 passes' ground,
+// but how many planes there are must not decide: results of a run over some planes
+// of a volume and of one over all of them stay equal.  Where few planes lose more
+// than many gain, the wave tiles take both.  (A line by the plane's size does not
+// tell the two apart.)  `alone`: one input plane set per launch (sequential updates,
+// single views).  Measured, µs per run of 10 iterations, two views of uint16,
+// wave tiles / float32:
+//   together, 11 taps: 1 plane of 512×512 208 / 275, 16 452 / 365, 64 1159 / 1009; of
+//     512×256 206 / 218, 317 / 247, 669 / 568 and 256 planes 1873 / 2298; of 512×1024 216 /
+//     493, 712 / 705, 2106 / 2655; 15 taps: 1, 16, 64 planes of 512×512 208 / 302, 450 /
+//     389, 1148 / 1076, of 104×640 209 / 494, 298 / 524, 597 / 570; rows below 256: 8, 64
+//     and 400 planes of 512×128 208 / 223, 439 / 457, 2413 / 2157;
+//   together, 41 taps (a launch each on the wave tiles): 256 planes of 512×512 8540 / 6482,
+//     248 of 171×87 1346 / 1089, 40 of 300×445 1692 / 1350, but 20 of 300×1030 1526 / 2721
+//     (strips with halo columns there);
+//   alone, 11 taps: 1, 16, 64 planes of 512×512 300 / 408, 564 / 480, 1525 / 1272; of rows
+//     that leave an eighth of their power-of-two work-group idle, 1, 16, 64 planes of
+//     512×640 305 / 470, 728 / 572, 1898 / 1688, of 104×640 299 / 529, 390 / 555, 717 / 614;
 //   alone, 21 taps: 128 planes of 512×512 3500 / 2949, 256 of 256×256 1612 / 1516, but 200 of
-//     384×384 3118 / 3638 (rows that leave an eighth of their power-of-two work-group
-//     idle), 16 of 1024×1024 1625 / 1688, 1000 of 128×128 1579 / 1545, 128 of them 411 / 505;
+//     384×384 3118 / 3638, 1, 8 and 64 planes of 512×1024 309 / 719, 572 / 782, 3427 / 3039,
+//     1000 of 128×128 1579 / 1545, 128 of them 411 / 505;
 //   alone, 31 taps: 64 of 512×512 1695 / 1654, 256 of 256×256 1598 / 1668, 100 of 512×768
-//     4474 / 4896; 41 taps: 256 of 256×256 2029 / 1881, 64 of 512×512 2100 / 1860, 64 of
-//     1000×1000 (float32) 8027 / 8032.
+//     4474 / 4896; 41 taps: 256 of 256×256 2029 / 1881, but 1, 8 and 64 of 512×512 407 / 626,
+//     588 / 664, 2148 / 1823.
 // Under the periodic boundary always (the tiles' chunks would cross the planes'
 // edges; read by elements they took 3867 µs against 1719, 64 planes of 512×512, two
 // views, 11 taps).
-bool float32_better(int Z, int X, int boundary, int k, bool alone) {
+bool float32_better(int X, int boundary, int k, bool alone) {
   if (boundary != MVD_BOUNDARY_ZERO) return true;
   int p2 = 1;
   while (p2 < X) p2 *= 2;
   const bool fills = X % 8 == 0 && 8 * X >= 7 * p2;
-  if (k > 33) return alone ? fills && X <= 512 : X <= 1024;
+  if (k > 33) return alone ? fills && X <= 256 : X <= 1024;
   if (X % 8 || X > 1024 || k > 21) return false;
-  const bool large = X >= 256 && (long)Z * X >= 1L << 16;
-  if (k <= 15) return large || (alone && fills);
+  if (k <= 15) return alone && fills;
   return alone && fills && X >= 256 && X <= 512;
 }
 
@@ -803,7 +801,7 @@ int march_bucket(const mvd_ctx *c, int boundary, int update) {
     if (w.sep_x) k = std::max({k, w.back.kz, w.back.kx});
   }
   const bool alone = c->nv == 1 || update == MVD_UPDATE_SEQUENTIAL;
-  return k >= kMarchMinTaps && !float32_better(c->Z, c->X, boundary, k, alone) ? sep_bucket(k) : 0;
+  return k >= kMarchMinTaps && !float32_better(c->X, boundary, k, alone) ? sep_bucket(k) : 0;
 }
 
 // The bucket of a single-input pass with kernels of k taps (the terms of low-rank

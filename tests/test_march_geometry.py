@@ -44,3 +44,29 @@ def test_forms_that_do_not_exist_are_refused(k, views, fused):
     st, _ = _plan(ctx, 1, k, views, fused)
     api.mvd_destroy(ctx)
     assert st == N.MVD_ERR_UNSUPPORTED
+
+
+SIM, SEQ = 0, 1
+
+
+@pytest.mark.parametrize("update,k,z,x,tiles", [
+    # few planes of these take up to three times as long on the float32 units, many
+    # of them at most a quarter less: wave tiles whatever the plane's size
+    (SIM, 9, 512, 384, True), (SIM, 15, 104, 640, True), (SIM, 15, 512, 512, True), (SIM, 11, 512, 1024, True),
+    (SEQ, 15, 104, 640, True), (SEQ, 11, 512, 384, True), (SEQ, 41, 512, 512, True), (SEQ, 41, 128, 480, True),
+    # one input per launch on rows that fill a power-of-two work-group
+    (SEQ, 11, 512, 512, False), (SEQ, 21, 128, 480, False), (SEQ, 41, 256, 256, False),
+    (SEQ, 31, 512, 512, True), (SIM, 31, 512, 512, True), (SIM, 41, 512, 512, False)])
+def test_units_do_not_depend_on_the_plane_s_size(update, k, z, x, tiles):
+    import numpy as np
+
+    f = N.lib().mvd_internal_wave_tiles
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    for rows in (z, 2 * z, 64):
+        d = api.Deconvolver(2, rows, x, N.MVD_DEVICE_NONE)
+        for v in range(2):
+            d.set_psf(v, np.full((k, k), 1.0 / (k * k), np.float32))
+        got = f(d.ctx, N.BOUNDARY["zero"], update)
+        d.close()
+        assert got == int(tiles)
